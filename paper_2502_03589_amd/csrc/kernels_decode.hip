@@ -1001,8 +1001,9 @@ __global__ __launch_bounds__(256, (decode_occupancy<BITS, PI, GT>())) void decod
         const __half* vt = c.v_tail + (((int64_t)s * H + hkv) * PI) * D + 8 * col;
         // The rows of a batch are requested together: one row at a time the wave waits out
         // PI/4 memory round trips in a row (7 sequences of 300-3001 tokens at partition 64:
-        // 21.0 -> 19.9 us a call).  Batch steps past the end are skipped as a whole;
-        // in the last one, lanes past the end read the last row with a zero weight.
+        // 21.0 -> 19.9 us a call).  Batch steps past the end are skipped as a whole; in the
+        // last one, lanes past the end read the last row and take it as zero (their p~, a
+        // masked token's, is zero too: times an infinite V value it would be NaN).
         constexpr int U = 8;
         const int nt = L - tb;
 #pragma unroll 1
@@ -1017,6 +1018,7 @@ __global__ __launch_bounds__(256, (decode_occupancy<BITS, PI, GT>())) void decod
           for (int u = 0; u < U; ++u) {
             if (e0 + 4 * u >= nt) break;
             const int e = e0 + 4 * u + grp;
+            if (e >= nt) raw[u] = uint4{0u, 0u, 0u, 0u};
             const __half2* h2 = reinterpret_cast<const __half2*>(&raw[u]);
             float vv[8];
 #pragma unroll
@@ -1027,15 +1029,13 @@ __global__ __launch_bounds__(256, (decode_occupancy<BITS, PI, GT>())) void decod
             }
 #pragma unroll
             for (int rt = 0; rt < GT; ++rt) {
-              const float4 p4 = *reinterpret_cast<const float4*>(&wl.ptail[rt][min(e, nt - 1)][0]);
+              const float4 p4 = *reinterpret_cast<const float4*>(&wl.ptail[rt][e][0]);
               const float4 f4 = *reinterpret_cast<const float4*>(&wl.tailf[rt][0]);
               const float pw[4] = {p4.x * f4.x, p4.y * f4.y, p4.z * f4.z, p4.w * f4.w};
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const float p = e < nt ? pw[i] : 0.0f;
+              for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) o_acc[rt][j][i] = fmaf(p, vv[j], o_acc[rt][j][i]);
-              }
+                for (int j = 0; j < 8; ++j) o_acc[rt][j][i] = fmaf(pw[i], vv[j], o_acc[rt][j][i]);
             }
           }
         }

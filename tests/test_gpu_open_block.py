@@ -42,3 +42,37 @@ def test_step_at_block_and_span_edges(bits, pi):
     case.lens = np.asarray(lens, np.int32) + 1
     assert np.array_equal(out_lens.cpu().numpy(), case.lens)
     assert gu.rel_err(got, O.attend_decode(case.q, case.oracle_seqs(), 2)) <= TOL
+
+
+def _infinite_case(gu, seed, lens, bits, pi, group):
+    """A cache whose every open block ends in a row with infinities in four channels (the
+    quantized blocks stay finite), and the oracle's sequences."""
+    case = gu.Case(seed, len(lens), 1, lens, bits, pi, group=group)
+    for b, n in enumerate(lens):
+        case.v[b, :, n - 1, [5, 64]] = np.inf
+        case.v[b, :, n - 1, [0, 127]] = -np.inf
+    return case.quantize()
+
+
+def _same_infinities(got, ref):
+    """The infinities of ref at their places with their signs; elsewhere the tolerance."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert inf.any() and np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf] > 0, ref[inf] > 0)
+    fin = np.isfinite(ref)
+    assert np.abs(got[fin] - ref[fin]).max() <= TOL * np.abs(ref[fin]).max()
+
+
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")  # the oracle's codes of the open block
+@pytest.mark.parametrize("bits,pi,group", [(2, 32, 4), (4, 32, 5), (2, 64, 1), (4, 64, 8), (2, 128, 3)])
+def test_decode_infinite_value_in_the_open_block(bits, pi, group):
+    """An infinite V value of the open block's last row, whatever the row's place in the batch
+    it is loaded in, gives infinite outputs in its channels and changes no other."""
+    import tests.gpu_util as gu
+    from paper_2502_03589_amd import hack as hk
+    lens = [4 * pi + t for t in OPEN[pi]] + [4 * pi + 2, pi - 1]
+    gu.announce(f"open block infinities bits={bits} pi={pi} G={group} lens={lens}")
+    case = _infinite_case(gu, 740 + bits + pi, lens, bits, pi, group)
+    got = hk.hack_attend_decode(case.layout, case.cache, torch.from_numpy(case.q).to(gu.DEV), case.lens_dev,
+                                case.max_len).cpu().numpy()
+    _same_infinities(got, O.attend_decode(case.q, case.oracle_seqs(), 1))
