@@ -648,11 +648,18 @@ __global__ __launch_bounds__(kGroupThreads* KG, 2) void prefill_kernel(PrefillAr
         }
       } else {
         // fp16 open block: O[row][ch] += sum_{t < T} p[row][t] v_t[ch] with unquantized p as
-        // three fp16 pieces under a factor 2^7 (p <= 2^8): exact to 2^-32 of p's scale
+        // three fp16 pieces under a factor 2^7 (p <= 2^8): exact to 2^-32 of p's scale.
+        // One tile's pieces at a time, and V rows by clamped index: the pieces of four tiles
+        // (partition 128) do not fit beside O, and a branch around each load made its wave wait
+        // for the load before (64 prompts of 60 tokens, 4 bits, partition 64: 63.7 -> 45.8 us;
+        // 100 tokens, 2 bits, 128: 29.3 -> 21.8).
+        // An infinite V value enters once, times whether the row gives the token weight: a
+        // piece of p may be zero where p is not, and infinity times that would be NaN.
         const __half* vt = c.v_tail + (((int64_t)s * c.kv_heads + hkv) * PI) * D;
-        u32x4 pb[NT][2][3];
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t) {
+          if (16 * t >= T) break;
+          u32x4 pb[2][3];
 #pragma unroll
           for (int g = 0; g < 2; ++g)
 #pragma unroll
@@ -669,32 +676,56 @@ __global__ __launch_bounds__(kGroupThreads* KG, 2) void prefill_kernel(PrefillAr
                 }
               }
 #pragma unroll
-              for (int k = 0; k < 3; ++k) pb[t][g][k][i] = w[k];
+              for (int k = 0; k < 3; ++k) pb[g][k][i] = w[k];
             }
 #pragma unroll 1
-        for (int jj = 0; jj < 4; ++jj) {
-          v16f acc = zero16();
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
+          for (int jj = 0; jj < 4; ++jj) {
+            u32x4 av[2];
+            uint32_t nonzero = 0u;  // sum of 0 v: zero unless some v is infinite
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
               const int tk = half * (PI / 2) + 16 * t + 8 * g;
-              uint16_t x[8];
+              av[g] = u32x4{0u, 0u, 0u, 0u};
+              if (16 * t + 8 * g < T) {
+                uint32_t x[8];
 #pragma unroll
-              for (int i = 0; i < 8; ++i)
-                x[i] = tk + i < T ? __half_as_ushort(vt[(int64_t)(tk + i) * D + 32 * jj + col]) : (uint16_t)0;
-              u32x4 av;
+                for (int i = 0; i < 8; ++i) x[i] = __half_as_ushort(vt[min(tk + i, T - 1) * D + 32 * jj + col]);
 #pragma unroll
-              for (int i = 0; i < 4; ++i) av[i] = (uint32_t)x[2 * i] | ((uint32_t)x[2 * i + 1] << 16);
+                for (int i = 0; i < 4; ++i) {
+                  av[g][i] = (tk + 2 * i < T ? x[2 * i] : 0u) | (tk + 2 * i + 1 < T ? x[2 * i + 1] << 16 : 0u);
+                  asm volatile("v_pk_fma_f16 %0, %1, 0, %0" : "+v"(nonzero) : "v"(av[g][i]));
+                }
+              }
+            }
+            v16f acc = zero16();
+            if (__builtin_amdgcn_ballot_w64(nonzero != 0u) != 0) {
 #pragma unroll
-              for (int k = 2; k >= 0; --k) acc = mfma_f16(av, pb[t][g][k], acc);
+              for (int g = 0; g < 2; ++g) {
+                u32x4 inf, one;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                  const uint32_t w = av[g][i];
+                  const uint32_t m = ((w & 0x7C00u) == 0x7C00u ? 0xFFFFu : 0u) |
+                                     ((w & 0x7C000000u) == 0x7C000000u ? 0xFFFF0000u : 0u);
+                  inf[i] = w & m;
+                  av[g][i] = w & ~m;
+                  one[i] = (sv[t][8 * g + 2 * i] > 0.0f ? 0x3C00u : 0u) |
+                           (sv[t][8 * g + 2 * i + 1] > 0.0f ? 0x3C000000u : 0u);
+                }
+                acc = mfma_f16(inf, one, acc);
+              }
             }
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (j == jj) {
+            for (int g = 0; g < 2; ++g)
 #pragma unroll
-              for (int i = 0; i < 16; ++i) o[j][i] = fmaf(acc[i], 0x1p-7f, o[j][i]);
-            }
+              for (int k = 2; k >= 0; --k) acc = mfma_f16(av[g], pb[g][k], acc);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (j == jj) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) o[j][i] = fmaf(acc[i], 0x1p-7f, o[j][i]);
+              }
+          }
         }
       }
     }

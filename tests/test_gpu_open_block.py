@@ -76,3 +76,31 @@ def test_decode_infinite_value_in_the_open_block(bits, pi, group):
     got = hk.hack_attend_decode(case.layout, case.cache, torch.from_numpy(case.q).to(gu.DEV), case.lens_dev,
                                 case.max_len).cpu().numpy()
     _same_infinities(got, O.attend_decode(case.q, case.oracle_seqs(), 1))
+
+
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+@pytest.mark.parametrize("bits,pi,group,L", [(2, 32, 4, 70), (4, 64, 2, 100), (2, 64, 4, 300), (4, 128, 1, 150)])
+def test_prefill_infinite_value_in_the_open_block(bits, pi, group, L):
+    """As in decode, where the weights are split into pieces of which some are zero: every row
+    that attends the token has infinite outputs in its channels, also the first one, whose
+    weight for it is about 2^-57; causal rows that end before the block are untouched."""
+    import tests.gpu_util as gu
+    from paper_2502_03589_amd import hack as hk
+    from paper_2502_03589_amd import synth
+    gu.announce(f"prefill open block infinities bits={bits} pi={pi} G={group} L={L}")
+    case = _infinite_case(gu, 760 + bits + pi + L, [L], bits, pi, group)
+    case.k[0, :, L - 1] = np.float16(-3.5)  # against a query of ones: a score of -39.6
+    case.quantize()
+    Q = synth.normal_f16(case.seed, "q", (1, case.Hq, L, case.d), sub=7)
+    Q[:, :, 0] = np.float16(1.0)
+    seqs = case.oracle_seqs()
+    got = hk.hack_attend_prefill(case.layout, case.cache, torch.from_numpy(Q).to(gu.DEV), False).cpu().numpy()
+    _same_infinities(got, O.attend_prefill(Q, seqs, 1, causal=False))
+    got = hk.hack_attend_prefill(case.layout, case.cache, torch.from_numpy(Q).to(gu.DEV), True).cpu().numpy()
+    last = [(0, h, L - 1) for h in range(case.Hq)]
+    ref = O.attend_prefill(Q, seqs, 1, causal=True, rows=last)
+    _same_infinities(np.stack([got[r] for r in last]), np.stack([ref[r] for r in last]))
+    case.v[0, :, L - 1] = 0  # not attended by the rows before the open block
+    early = L // pi * pi // 32 * 32
+    ref = O.attend_prefill(Q, case.oracle_seqs(), 1, causal=True)[:, :, :early]
+    assert gu.rel_err(got[:, :, :early], ref) <= TOL
