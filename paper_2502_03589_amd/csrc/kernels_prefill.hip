@@ -483,13 +483,13 @@ __global__ __launch_bounds__(kGroupThreads* KG, 2) void prefill_kernel(PrefillAr
               const int e = 16 * j + code_element<BITS>(q, b);
               const float t = __fmul_rn(__fsub_rn(x[e], mn), r);
               int code = 0;
-              if (s32 != 0.0f) {
-                if constexpr (SR) {
-                  const float u = sr_threshold(a.key_q, qp_index(s, a.num_q_heads, hq, row, c0 + e));
-                  code = (int)round_stochastic(t, u, a.qmax);
-                } else {
-                  code = (int)fminf(rintf(t), a.qmax);
-                }
+              // Stochastic: on every lane (t = 0 and so the code is 0 where s32 = 0).  A branch a
+              // value that leaves few rows in it lowers the clock (36 tokens: 25.2 us; all: 15.1).
+              if constexpr (SR) {
+                const float u = sr_threshold(a.key_q, qp_index(s, a.num_q_heads, hq, row, c0 + e));
+                code = (int)round_stochastic(t, u, a.qmax);
+              } else if (s32 != 0.0f) {
+                code = (int)fminf(rintf(t), a.qmax);
               }
               csum += code;
               v |= (uint32_t)((code - a.qoff) & 0xFF) << (8 * b);
@@ -798,10 +798,12 @@ static hipError_t prefill_impl(const PrefillArgs& a, bool stochastic, hipStream_
   // chain over share, one group -> two): 1500 tokens causal 2.6, 75.8 -> 63.0 us; 4 x 1000 at
   // partition 128 1.8, 68.8 -> 63.2; 512 tokens 7.1, 25.3 -> 22.9; but 3000 tokens 1.3, 136 ->
   // 158, and chains of two or three blocks lose more to the merge than they gain (63 tokens,
-  // 14.1 -> 16.1).
+  // 14.1 -> 16.1).  With stochastic rounding each group also draws the thresholds of Q, 64 a
+  // lane: chains below ten blocks lose (100 tokens at partition 32, 20.7 -> 24.6 us; 300 at 64,
+  // 34.4 -> 36.9; 640 at 128, 47.3 -> 49.8), longer ones gain (640 at 32, 65.2 -> 59.5).
   const int64_t blocks = ((int64_t)a.len + PI - 1) / PI;
   const int64_t share = (wgs * (a.causal ? blocks + 1 : 2 * blocks) / 2 + kSlots - 1) / kSlots;
-  const bool two = blocks >= 4 && 5 * blocks > 8 * share;
+  const bool two = blocks >= (stochastic ? 10 : 4) && 5 * blocks > 8 * share;
   const dim3 threads(kGroupThreads * (two ? 2 : 1));
   if (stochastic) {
     if (two) hipLaunchKernelGGL((prefill_kernel<BITS, PI, true, 2>), grid, threads, 0, stream, a);

@@ -70,3 +70,20 @@ def test_prefill_wide_key_and_value_ranges():
         print(f"rows: median {np.median(rows):.2e} 90% {np.quantile(rows, 0.9):.2e} max {rows.max():.2e}")
         assert np.quantile(rows, 0.9) <= 1e-4
         assert gu.rel_err(got, ref) <= TOL
+
+
+@pytest.mark.parametrize("bits,pi,L,qp", [(2, 32, 33, 8), (4, 64, 66, 4), (2, 128, 129, 8)])
+def test_prefill_stochastic_few_rows_and_constant_partitions(bits, pi, L, qp):
+    """Stochastic Q codes are drawn on every lane: the last row block holds one or two rows, and
+    constant partitions (scale 0, code 0 whatever the threshold) lie among the others."""
+    import tests.gpu_util as gu
+    from paper_2502_03589_amd import hack as hk
+    from paper_2502_03589_amd import synth
+    gu.announce(f"prefill stochastic rows bits={bits} pi={pi} L={L} qp={qp}")
+    case = gu.Case(980 + bits + pi, 1, 2, [L], bits, pi, group=3, rounding=O.STOCHASTIC, qp_bits=qp).quantize()
+    Q = synth.normal_f16(case.seed, "q", (1, case.Hq, L, case.d), sub=7)
+    Q[:, 1, ::3, :pi] = np.float16(0.5)
+    Q[:, 4, L - 1] = np.float16(-0.25)
+    got = hk.hack_attend_prefill(case.layout, case.cache, torch.from_numpy(Q).to(gu.DEV), True).cpu().numpy()
+    ref = O.attend_prefill(Q, case.oracle_seqs(), 2, causal=True, qp_bits=qp, stochastic_seed=case.seed)
+    assert gu.rel_err(got, ref) <= TOL
