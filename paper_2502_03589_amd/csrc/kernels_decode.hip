@@ -1169,9 +1169,23 @@ DecodePlan plan_decode(const hack_kv_layout& lay, int batch, int num_q_heads, in
   const int64_t spans_seq = ((int64_t)max_len + span - 1) / span;
   int64_t wg_spans = pairs > 0 ? (spans_seq * pairs * nhg + target - 1) / target : 1;
   // At least one span per wave: a chunk of fewer spans leaves waves idle and adds chunks to
-  // merge, at the same time per span (one sequence of 256 tokens: 8.2 us a call in two
-  // one-span chunks, 7.0 in one).
-  wg_spans = std::max<int64_t>(wg_spans, std::min<int64_t>(kWaves, std::max<int64_t>(spans_seq, 1)));
+  // merge, at nearly the same time per span (device time of one sequence, 1 head, of 256 tokens,
+  // partition 32: 7.6 us in two one-span chunks, 5.8 in one; 32/8 heads, 4096 tokens: 15.4 in 32
+  // chunks, 10.2 in 8).  Two exceptions:
+  // - Five to eight spans of few (sequence, head) groups: the second of two chunks runs its wave
+  //   of the last, partial span after the others' code, and four chunks are merged as fast as
+  //   two (4 bits, partition 64, 32/8 heads, 1280 tokens: chunks of 1 / 2 / 4 spans 10.6 / 10.5 /
+  //   11.4 us; from 64 groups on 2 and 4 are level, 12.1 to 11.9).
+  // - An even share of three spans fills the chip: chunks of four leave more spans to the
+  //   fullest compute unit where the workgroups are rounded up (7 sequences, 64/8 heads, 3001
+  //   tokens, 2 bits, partition 64: 16.0 us in chunks of three, 17.1 in chunks of four).
+  int64_t least = kWaves;
+  const auto fullest = [&](int64_t n) {  // spans of the fullest compute unit with chunks of n
+    return ((spans_seq + n - 1) / n * pairs * nhg + kComputeUnits - 1) / kComputeUnits * n;
+  };
+  if (spans_seq > kWaves && spans_seq <= 2 * kWaves && pairs * nhg < 64) least = 2;
+  else if (wg_spans == 3 && fullest(3) < fullest(4)) least = 3;
+  wg_spans = std::max<int64_t>(wg_spans, std::min<int64_t>(least, std::max<int64_t>(spans_seq, 1)));
   // A chunk of at most kFillWgSpans spans bounds the time one workgroup holds a slot:
   // in a ragged batch the longest sequences then spread over more workgroups than an
   // even share of the mean length would give them.  When the even share at max_len is

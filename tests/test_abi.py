@@ -201,6 +201,26 @@ def test_decode_chunk_plan(lib, bits, batch, hq, max_len, splits):
     assert _planned_splits(ws, pairs, group, (group + 3) // 4) == splits
 
 
+@pytest.mark.parametrize("bits,pi,batch,hq,hkv,max_len,splits", [
+    (2, 32, 1, 1, 1, 256, 1),     # two spans: one chunk, nothing to merge
+    (2, 32, 16, 16, 2, 512, 1),   # four spans, one a wave
+    (4, 64, 1, 32, 8, 1280, 3),   # five spans of 8 groups: chunks of two
+    (2, 32, 4, 32, 8, 1000, 4),   # eight spans of 32 groups
+    (2, 32, 16, 16, 2, 1024, 2),  # eight spans of 64 groups: one span a wave again
+    (2, 32, 1, 32, 8, 4096, 8),   # 32 spans: one span a wave
+    (2, 64, 7, 64, 8, 3001, 4),   # even share of three spans: 448 workgroups of three, not 336 of four
+    (2, 32, 32, 32, 8, 4096, 3),  # even share of eleven spans: kept
+])
+def test_decode_short_chunk_plan(lib, bits, pi, batch, hq, hkv, max_len, splits):
+    """Chunks of short sequences: a span per wave (four), fewer only for five to eight spans of
+    few groups and where an even share of three spans fills the chip better."""
+    lay = hk.hack_kv_layout_make(128, hkv, bits, pi, 4 * pi)
+    pairs, group = batch * hkv, hq // hkv
+    up = lambda n: -(-n // 256) * 256
+    ws = hk.hack_decode_workspace_bytes(lay, batch, hq, max_len)
+    assert ws == up(pairs * ((group + 3) // 4) * 4) + up(pairs * splits * group * (4 + 128) * 4)
+
+
 def test_status_strings(lib):
     for st in range(6):
         assert len(hk.hack_status_string(st)) > 0
