@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "hack_internal.hpp"
+#include "launch_rules.hpp"
 
 namespace hack {
 
@@ -276,6 +277,7 @@ struct PrefillArgs {
   int causal;
   int nqb;           // row blocks of 32 * 4 / HW rows
   int batch;
+  int grid_x, workgroups;  // workgroup index = x + y grid_x, below workgroups
   float qmax;        // 2^b_QP - 1 of the transient Q and P codes (15 or 255)
   float inv_qmax;    // 1 / qmax
   int qoff;          // Q codes enter the signed int8 MFMA as code - qoff, qoff = 2^(b_QP - 1)
@@ -399,7 +401,9 @@ __global__ __launch_bounds__(kGroupThreads* KG, 2) void prefill_kernel(PrefillAr
   // to run alone at the end (row blocks fastest: 952 us for 8192 tokens, 1.4 waves per SIMD
   // resident), and with a multiple of eight heads an XCD's L2 sees one kv head's blocks.
   const int nh = c.kv_heads * a.head_groups;
-  const int hk = (int)blockIdx.x % nh, sq_qb = (int)blockIdx.x / nh;
+  const int wg = (int)blockIdx.y * a.grid_x + (int)blockIdx.x;
+  if (wg >= a.workgroups) return;
+  const int hk = wg % nh, sq_qb = wg / nh;
   const int hkv = hk % c.kv_heads, hg = hk / c.kv_heads;
   const int s = sq_qb % a.batch;
   const int hw = 1 << a.hw_log2;
@@ -785,25 +789,16 @@ __global__ __launch_bounds__(kGroupThreads* KG, 2) void prefill_kernel(PrefillAr
   }
 }
 
-constexpr int kSlots = 512;  // four-wave workgroups resident at two waves per SIMD
-
 template <int BITS, int PI>
-static hipError_t prefill_impl(const PrefillArgs& a, bool stochastic, hipStream_t stream) {
+static hipError_t prefill_impl(PrefillArgs& a, bool stochastic, hipStream_t stream) {
+  const PrefillGrid g =
+      prefill_grid(a.nqb, a.c.kv_heads * a.head_groups, a.batch, a.len, PI, a.causal != 0, stochastic);
   // at least 768 bytes of queries and outputs each: the count stays far below 2^31
-  const int64_t wgs = (int64_t)a.nqb * a.c.kv_heads * a.head_groups * a.batch;
-  if (wgs > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)wgs);
-  // A grid runs at the pace of its longest chain of blocks where that is longer than a
-  // workgroup slot's even share of all blocks; two key groups halve it.  Measured (32/8 heads,
-  // chain over share, one group -> two): 1500 tokens causal 2.6, 75.8 -> 63.0 us; 4 x 1000 at
-  // partition 128 1.8, 68.8 -> 63.2; 512 tokens 7.1, 25.3 -> 22.9; but 3000 tokens 1.3, 136 ->
-  // 158, and chains of two or three blocks lose more to the merge than they gain (63 tokens,
-  // 14.1 -> 16.1).  With stochastic rounding each group also draws the thresholds of Q, 64 a
-  // lane: chains below ten blocks lose (100 tokens at partition 32, 20.7 -> 24.6 us; 300 at 64,
-  // 34.4 -> 36.9; 640 at 128, 47.3 -> 49.8), longer ones gain (640 at 32, 65.2 -> 59.5).
-  const int64_t blocks = ((int64_t)a.len + PI - 1) / PI;
-  const int64_t share = (wgs * (a.causal ? blocks + 1 : 2 * blocks) / 2 + kSlots - 1) / kSlots;
-  const bool two = blocks >= (stochastic ? 10 : 4) && 5 * blocks > 8 * share;
+  if (g.workgroups > 0x7FFFFFFF) return hipErrorInvalidValue;
+  a.grid_x = (int)g.x;
+  a.workgroups = (int)g.workgroups;
+  const dim3 grid((unsigned)g.x, (unsigned)g.y);
+  const bool two = g.groups == 2;
   const dim3 threads(kGroupThreads * (two ? 2 : 1));
   if (stochastic) {
     if (two) hipLaunchKernelGGL((prefill_kernel<BITS, PI, true, 2>), grid, threads, 0, stream, a);

@@ -4,7 +4,7 @@
 // The projection is one GEMM: out[token][n] = sum_i E[token][i] W[n][i], where the
 // output channels n are the H_q query heads' 128 channels, then the H_kv key heads',
 // then the H_kv value heads'.  One workgroup of four or eight 64-lane waves computes a tile
-// of one or two heads of 32 to 256 tokens of one sequence (choose_tile):
+// of one or two heads of 32 to 256 tokens of one sequence (choose_project_tile):
 //   main loop  K steps of 32 or 64 input channels through three or four LDS stages (the E
 //              rows and the W rows of the step, 16-byte chunks XOR-swizzled so that fragment
 //              reads hit distinct banks).  The stages are filled by direct global-to-LDS loads
@@ -26,6 +26,7 @@
 // W tiles (groups of four token tiles per channel tile, contiguous ranges per XCD), so
 // each slab is fetched into that XCD's L2 once for several workgroups.
 #include "hack_internal.hpp"
+#include "launch_rules.hpp"
 
 namespace hack {
 
@@ -289,66 +290,30 @@ __global__ __launch_bounds__(Shape::kThreads, 1) void project_kernel(ProjectArgs
   }
 }
 
-template <int BITS, int PI, class Shape>
+template <int BITS, int PI, int INDEX, class Shape>
 static hipError_t project_tile(ProjectArgs& a, hipStream_t stream) {
+  constexpr ProjectTile t = kProjectTiles[INDEX];
+  static_assert(t.bm == Shape::BM && t.bn == Shape::BN && t.threads == Shape::kThreads, "the rule's tile");
   a.mtiles = (a.len + Shape::BM - 1) / Shape::BM;
   a.ntiles = (a.nheads * 128 + Shape::BN - 1) / Shape::BN;
-  a.total = (int64_t)a.batch * a.mtiles * a.ntiles;
-  if (a.total > 0x7FFFFFFF) return hipErrorInvalidValue;
+  a.total = project_workgroups(t, a.batch, a.len, a.nheads);
+  if (a.total * Shape::kThreads > kMaxLaunchThreads) return hipErrorInvalidValue;
   hipLaunchKernelGGL((project_kernel<BITS, PI, Shape>), dim3((unsigned)a.total), dim3(Shape::kThreads), 0, stream, a);
   return hipGetLastError();
 }
 
-// Tile shapes, and what w rounds of one workgroup per compute unit of them take in
-// microseconds at hidden 4096 (all of it scales with hidden): offset + per_round * w.  Measured
-// with 48 output heads:
-//   tokens      16/64   250    512   1024   1500   2048   3000   4096   8192
-//   32 x 128     20.6   30.8   49.4   93
-//   64 x 128     27.5   28.3   39.3   77    112    131    193    253    497
-//   128 x 128    36     37.5   38.0   86    123    132    202    252    487
-//   256 x 128    54     58.7   58.4   62.4  123    127    187    212    409
-//   256 x 256    91    103    102    104    106    117    222    228    380
-// Small tiles put a short prompt on more compute units (its weights are a latency-bound stream
-// of three to four steps in flight per workgroup); large ones fetch E and W fewer times
-// (the stream from L2 bounds a full chip).  A V block lies in one tile, so partitions of 64
-// and 128 start at tiles of as many tokens.
-struct TileCost {
-  int bm, bn;
-  float offset, per_round;
-};
-constexpr TileCost kTiles[] = {
-    {32, 128, 6.0f, 14.5f}, {64, 128, 6.0f, 22.0f}, {128, 128, 0.0f, 40.0f}, {256, 128, 0.0f, 65.0f}, {256, 256, 0.0f, 115.0f}};
-constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
-constexpr int kComputeUnits = 256;
-
-static int choose_tile(const ProjectArgs& a, int partition) {
-  int best = kTileCount - 1;
-  float least = 0.0f;
-  for (int i = kTileCount - 1; i >= 0 && kTiles[i].bm >= partition; --i) {
-    const int64_t tiles = (int64_t)a.batch * ((a.len + kTiles[i].bm - 1) / kTiles[i].bm) *
-                          ((a.nheads * 128 + kTiles[i].bn - 1) / kTiles[i].bn);
-    if (tiles > 0x7FFFFFFF) continue;
-    const float t = kTiles[i].offset + kTiles[i].per_round * (float)((tiles + kComputeUnits - 1) / kComputeUnits);
-    if (least == 0.0f || t < least) {
-      best = i;
-      least = t;
-    }
-  }
-  return best;
-}
-
 template <int BITS, int PI>
 static hipError_t project_impl(ProjectArgs& a, hipStream_t stream) {
-  switch (choose_tile(a, PI)) {
+  switch (choose_project_tile(a.batch, a.len, a.nheads, PI)) {
     case 0:
-      if constexpr (PI <= 32) return project_tile<BITS, PI, Tile<32, 128, 1, 4, 64, 4>>(a, stream);
+      if constexpr (PI <= 32) return project_tile<BITS, PI, 0, Tile<32, 128, 1, 4, 64, 4>>(a, stream);
       return hipErrorInvalidValue;
     case 1:
-      if constexpr (PI <= 64) return project_tile<BITS, PI, Tile<64, 128, 2, 2, 64, 3>>(a, stream);
+      if constexpr (PI <= 64) return project_tile<BITS, PI, 1, Tile<64, 128, 2, 2, 64, 3>>(a, stream);
       return hipErrorInvalidValue;
-    case 2: return project_tile<BITS, PI, Tile<128, 128, 2, 4, 64, 4>>(a, stream);
-    case 3: return project_tile<BITS, PI, Tile<256, 128, 4, 2, 64, 3>>(a, stream);
-    default: return project_tile<BITS, PI, Tile<256, 256, 2, 4, 32, 4>>(a, stream);
+    case 2: return project_tile<BITS, PI, 2, Tile<128, 128, 2, 4, 64, 4>>(a, stream);
+    case 3: return project_tile<BITS, PI, 3, Tile<256, 128, 4, 2, 64, 3>>(a, stream);
+    default: return project_tile<BITS, PI, 4, Tile<256, 256, 2, 4, 32, 4>>(a, stream);
   }
 }
 

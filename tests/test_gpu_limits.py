@@ -72,3 +72,28 @@ def test_prefill_at_the_batch_limit():
     err = float(np.abs(g - r).max() / np.abs(r).max())
     print(f"sampled rows max|d|/|O|inf = {err:.3e}")
     assert err <= TOL
+
+
+def test_prefill_grid_of_two_dimensions():
+    """More workgroups (65535 sequences x 65 heads = 4.26 million) than one row of the grid holds.
+    Prompts of one token attend it alone, so every output row is that token's V row, exactly;
+    the sequences share one page and differ in their open blocks."""
+    gu = _gpu()
+    from paper_2502_03589_amd import hack as hk
+    H, d = 65, 128
+    gu.announce(f"prefill batch={B_MAX} L=1 heads={H}/{H} bits=2 pi=32")
+    lay = hk.hack_kv_layout_make(d, H, 2, 32, 128)
+    table = torch.zeros((B_MAX, 1), dtype=torch.int32, device=gu.DEV)
+    cache = hk.KVCache(lay, 1, B_MAX, table, gu.DEV)
+    g = torch.Generator(device=gu.DEV)
+    g.manual_seed(2026)
+    k = torch.randn((1, H, 1, d), generator=g, device=gu.DEV).half()
+    one = torch.ones(1, dtype=torch.int32, device=gu.DEV)
+    hk.hack_quantize(lay, cache, k, k, one)  # the shared page's K row
+    tail = cache.buffers["v_tail"].view(torch.float16)[:B_MAX * H * 32 * d].view(B_MAX, H, 32, d)
+    v = torch.randn((B_MAX, H, d), generator=g, device=gu.DEV).half()
+    tail[:, :, 0].copy_(v)
+    q = torch.randn((B_MAX, H, 1, d), generator=g, device=gu.DEV).half()
+    out = hk.hack_attend_prefill(lay, cache, q, True)
+    # p = 1 as 128 = 2^7 in three fp16 pieces, times v, times 2^-7 / 1: exact
+    assert torch.equal(out[:, :, 0], v.float())
