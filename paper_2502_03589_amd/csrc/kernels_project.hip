@@ -304,7 +304,7 @@ static hipError_t project_tile(ProjectArgs& a, hipStream_t stream) {
 
 template <int BITS, int PI>
 static hipError_t project_impl(ProjectArgs& a, hipStream_t stream) {
-  switch (choose_project_tile(a.batch, a.len, a.nheads, PI)) {
+  switch (choose_project_tile(a.batch, a.len, a.nheads, a.hidden, PI)) {
     case 0:
       if constexpr (PI <= 32) return project_tile<BITS, PI, 0, Tile<32, 128, 1, 4, 64, 4>>(a, stream);
       return hipErrorInvalidValue;

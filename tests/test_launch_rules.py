@@ -1,5 +1,5 @@
 """Host rules of the prefill and projection launches (launch_rules.hpp), compiled for the CPU:
-grids stay within a launch's limits."""
+grids stay within a launch's limits, and the projection's tile is the fastest one measured."""
 import os
 import shutil
 import subprocess
@@ -22,7 +22,7 @@ int main() {
     if (kind == 'p') {
       int b, l, h, hid, p;
       if (std::scanf("%d %d %d %d %d", &b, &l, &h, &hid, &p) != 5) return 1;
-      const hack::ProjectTile& t = hack::kProjectTiles[hack::choose_project_tile(b, l, h, p)];
+      const hack::ProjectTile& t = hack::kProjectTiles[hack::choose_project_tile(b, l, h, hid, p)];
       std::printf("%d %d %d %lld\n", t.bm, t.bn, t.threads, (long long)hack::project_workgroups(t, b, l, h));
     } else {
       int r, h, b, l, p, c, s;
@@ -85,3 +85,72 @@ def test_projection_tile_fits_the_grid_wherever_the_largest_does(rules, heads, b
     assert bm >= partition and bm % 32 == 0
     if largest <= MAX_THREADS:
         assert n * threads <= MAX_THREADS
+
+
+TILES = [(32, 128), (64, 128), (128, 128), (256, 128), (256, 256)]
+# tokens -> us of 32 x 128, 64 x 128, 128 x 128, 256 x 128, 256 x 256 tiles (partition 32)
+MEASURED = {  # (batch, output heads, hidden)
+    (1, 20, 1024): {
+        64: (9.6, 11.6, 14.2, 18.8, 32.1),
+        250: (10.5, 12.3, 15.2, 23.3, 41.5),
+        350: (10.9, 12.7, 15.6, 23.3, 41.1),
+        512: (12.2, 12.3, 15.0, 23.3, 41.1),
+        1000: (19.2, 15.3, 15.7, 23.6, 41.2),
+        1500: (21.8, 17.2, 17.7, 25.4, 42.8),
+        3000: (38.4, 28.3, 29.7, 28.5, 45.8),
+    },
+    (1, 48, 1024): {
+        64: (9.9, 11.8, 14.5, 19.3, 32.5),
+        250: (13.0, 13.0, 15.8, 23.8, 42.0),
+        350: (21.3, 15.6, 16.3, 23.9, 41.4),
+        512: (21.1, 16.1, 16.1, 24.1, 41.7),
+        1000: (34.0, 27.2, 30.4, 25.6, 42.7),
+        1500: (46.2, 37.6, 42.1, 44.2, 45.9),
+        3000: (85.9, 61.9, 68.6, 63.6, 76.5),
+    },
+    (2, 36, 1024): {
+        64: (9.9, 11.8, 14.5, 19.4, 32.6),
+        250: (19.9, 15.4, 16.2, 24.0, 42.0),
+        350: (23.2, 16.8, 16.9, 24.6, 42.0),
+        512: (28.6, 24.7, 28.0, 24.5, 41.8),
+        1000: (43.8, 35.7, 39.3, 42.1, 45.3),
+        1500: (63.2, 46.4, 52.1, 44.2, 50.2),
+        3000: (117.1, 83.4, 89.3, 81.4, 83.9),
+    },
+    (1, 20, 4096): {
+        64: (21.6, 28.0, 36.7, 53.7, 90.8),
+        250: (22.9, 29.3, 38.2, 59.0, 101.0),
+        350: (23.8, 29.9, 38.9, 59.4, 100.6),
+        512: (30.9, 30.1, 38.5, 59.5, 101.7),
+        1000: (50.2, 37.5, 41.5, 60.0, 101.5),
+        1500: (65.6, 45.9, 50.2, 70.2, 107.7),
+        3000: (118.5, 81.9, 89.8, 75.3, 115.3),
+    },
+    (1, 48, 4096): {
+        64: (22.5, 28.8, 37.6, 55.3, 91.5),
+        250: (32.7, 31.0, 39.5, 59.8, 102.8),
+        350: (51.3, 36.4, 40.1, 60.3, 100.9),
+        512: (53.7, 40.8, 43.7, 63.3, 102.2),
+        1000: (95.2, 75.2, 86.4, 65.2, 104.4),
+        1500: (134.3, 110.4, 121.8, 123.2, 115.9),
+        3000: (268.4, 195.0, 216.4, 194.0, 224.2),
+    },
+    (2, 36, 4096): {
+        64: (22.3, 28.6, 37.8, 55.4, 91.5),
+        250: (50.6, 37.6, 40.8, 60.5, 102.3),
+        350: (61.9, 42.4, 44.6, 65.8, 103.0),
+        512: (78.9, 70.3, 79.8, 62.6, 103.1),
+        1000: (136.4, 111.4, 121.7, 123.3, 111.2),
+        1500: (202.8, 148.8, 162.5, 132.4, 127.0),
+        3000: (392.4, 277.3, 300.0, 260.0, 241.4),
+    },
+}
+
+
+@pytest.mark.parametrize("key", sorted(MEASURED))
+def test_projection_tile_is_the_fastest_measured(rules, key):
+    """Within 6% of the fastest shape (5% is what one shape's time moves between runs)."""
+    batch, heads, hidden = key
+    for length, times in MEASURED[key].items():
+        tile = rules("p", batch, length, heads, hidden, 32)[:2]
+        assert times[TILES.index(tile)] <= 1.06 * min(times), (length, tile)
