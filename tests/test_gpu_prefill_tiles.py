@@ -87,3 +87,42 @@ def test_prefill_stochastic_few_rows_and_constant_partitions(bits, pi, L, qp):
     got = hk.hack_attend_prefill(case.layout, case.cache, torch.from_numpy(Q).to(gu.DEV), True).cpu().numpy()
     ref = O.attend_prefill(Q, case.oracle_seqs(), 2, causal=True, qp_bits=qp, stochastic_seed=case.seed)
     assert gu.rel_err(got, ref) <= TOL
+
+
+SAMPLED = [
+    # Four V blocks or more.  bits, pi, q_heads, kv_heads, batch, length, causal, rounding, page, key groups
+    (2, 32, 32, 8, 2, 1999, True, 0, 256, 1),     # open block, pages
+    (4, 32, 8, 8, 24, 190, True, 1, 0, 1),        # stochastic codes, a head to a workgroup
+    (4, 64, 16, 2, 24, 300, True, 1, 64, 1),      # stochastic codes, pages, open block
+    (2, 64, 4, 4, 60, 300, False, 0, 0, 1),       # no mask
+    (4, 128, 8, 2, 30, 600, False, 0, 0, 1),      # no mask, open block
+    (2, 128, 2, 1, 40, 650, True, 0, 128, 1),     # two heads to a workgroup, pages
+    (2, 32, 8, 1, 60, 150, True, 0, 0, 1),
+    (2, 128, 8, 2, 16, 640, True, 1, 0, 1),       # stochastic codes, whole blocks
+    (2, 32, 8, 2, 1, 700, True, 1, 32, 2),        # stochastic codes in two key groups
+    (4, 64, 4, 1, 1, 1000, True, 1, 0, 2),
+]
+
+
+@pytest.mark.parametrize("bits,pi,hq,hkv,B,L,causal,rounding,page,groups", SAMPLED)
+def test_prefill_sampled_rows_of_larger_grids(bits, pi, hq, hkv, B, L, causal, rounding, page, groups):
+    """Chains of several blocks in one key group of waves (a full grid) and in two (a short one);
+    that each case takes the number beside it is checked on the CPU with the launch rules."""
+    import tests.gpu_util as gu
+    from paper_2502_03589_amd import hack as hk
+    from paper_2502_03589_amd import synth
+    gu.announce(f"prefill sampled bits={bits} pi={pi} heads={hq}/{hkv} B={B} L={L} causal={causal} page={page} "
+                f"rounding={rounding}")
+    case = gu.Case(1100 + bits + pi + L, B, hkv, [L] * B, bits, pi, group=hq // hkv, paged_page=page,
+                   rounding=rounding).quantize()
+    Q = synth.normal_f16(case.seed, "q", (B, hq, L, case.d), sub=7)
+    got = hk.hack_attend_prefill(case.layout, case.cache, torch.from_numpy(Q).to(gu.DEV), causal).cpu().numpy()
+    g = np.random.default_rng(L)
+    rows = [(0, 0, 0), (B - 1, hq - 1, L - 1), (0, hq - 1, L // pi * pi - 1), (B - 1, 0, L // 2)]
+    rows += [(int(g.integers(B)), int(g.integers(hq)), int(g.integers(L))) for _ in range(28)]
+    group = hq // hkv
+    ref = O.attend_prefill(Q, case.oracle_seqs({(b, h // group) for b, h, _ in rows}), hkv, causal=causal, rows=rows,
+                           stochastic_seed=case.seed if rounding else None)
+    g = np.stack([got[r] for r in rows])
+    r = np.stack([ref[r] for r in rows])
+    assert np.abs(g - r).max() <= TOL * np.abs(r).max()

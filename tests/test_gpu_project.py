@@ -107,9 +107,9 @@ def test_project_bit_exact_where_the_projection_is_exact(bits, pi, paged, roundi
 
 @pytest.mark.parametrize("B,Hkv,G,bits,pi,L", [(1, 1, 3, 2, 32, 300), (2, 3, 1, 4, 64, 520)])
 def test_project_odd_head_counts_bit_exact(B, Hkv, G, bits, pi, L):
-    """Output heads are computed two to a tile: 5 and 9 heads give tiles that mix a query
-    and a key head, and a last tile with a single value head (its second half reads
-    clamped weight rows and is never stored)."""
+    """Odd numbers of output heads (5 and 9) on tiles of one head.  (Tiles of two heads that mix a
+    query and a key head, or end in a single value head, take longer prompts: see the deep
+    projection among the tile-shape tests.)"""
     gu = _gpu()
     from paper_2502_03589_amd import hack as hk
     gu.announce(f"project odd heads B={B} Hkv={Hkv} G={G} bits={bits} pi={pi} L={L}")

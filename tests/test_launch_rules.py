@@ -154,3 +154,23 @@ def test_projection_tile_is_the_fastest_measured(rules, key):
     for length, times in MEASURED[key].items():
         tile = rules("p", batch, length, heads, hidden, 32)[:2]
         assert times[TILES.index(tile)] <= 1.06 * min(times), (length, tile)
+
+
+def test_gpu_tests_reach_the_tiles_they_name(rules):
+    from tests import test_gpu_project_tiles as gpu
+    seen = set()
+    for (bits, pi, B, Hq, H, lengths, page, rounding), tile in zip(gpu.CASES, gpu.TILES):
+        for length in lengths:
+            assert rules("p", B, length, Hq + 2 * H, 192, pi)[:2] == tile, (Hq, H, length)
+    for bits, pi, B, Hq, H, length, page, rounding, tile in gpu.DEEP:
+        assert rules("p", B, length, Hq + 2 * H, 4096, pi)[:2] == tile, (Hq, H, length)
+        seen.add(tile)
+    assert seen == set(TILES)
+
+
+def test_gpu_tests_reach_both_key_group_counts(rules):
+    from tests import test_gpu_prefill_tiles as gpu
+    for bits, pi, hq, hkv, B, length, causal, rounding, page, groups in gpu.SAMPLED:
+        rows, heads = attention_rows(hq, hkv, length)
+        assert rules("a", rows, heads, B, length, pi, int(causal), rounding)[3] == groups, (hq, hkv, B, length)
+        assert -(-length // pi) >= 4
