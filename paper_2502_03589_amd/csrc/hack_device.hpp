@@ -232,7 +232,9 @@ __device__ __forceinline__ void append_v_channel(const CacheView& c, int s, int 
 // depend on the sequence's length, so they are loaded (load) before it is known and the
 // two memory round trips overlap; store writes the token at position L, 0 <= L < capacity.
 // A K partition of 64 channels is loaded in store: its 32 registers held over the length's
-// load put the 4-bit decode kernel over 256 (24 bytes of scratch).
+// load put 24 bytes of the 4-bit decode kernel into scratch.  (8 are left there, two values
+// stored and one reloaded once per masked span, since the open block's rows are batched; the
+// stochastic variant keeps 16 registers there.)
 template <int BITS, int PI>
 struct AppendRegs {
   static constexpr int D = 128, P = D / PI;

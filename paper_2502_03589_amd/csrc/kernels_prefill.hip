@@ -132,6 +132,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f{lo, hi}), v2b));
 }
 // x as three bf16 values x1 + x2 + x3 (exact; the last two remainders are exact in fp32).
+// Rounded, not cut (cut_bf16): x2 and x3 are half as large and of either sign, which the scale
+// products' error below rests on.  The rank-1 products take all products of their pieces but the
+// smallest, so truncation, one instruction a piece instead of three, serves them as well.
 struct Pieces {
   float x1, x2, x3;
 };
@@ -438,8 +441,11 @@ __global__ __launch_bounds__(kGroupThreads* KG, 2) void prefill_kernel(PrefillAr
   // ---- Q row: codes per partition (float32 metadata), in MFMA operand layout: this lane
   // holds channels [p PI + half PI/2, + PI/2) of each partition p ----
   v4i qop[P][NJ];
-  // Partition 128 at 4 bits spills; its rank-1 operand is rebuilt for every tile from one
-  // register (28/4 heads, 1100 tokens: 66.9 us with the operand kept, 63.8 rebuilt).
+  // Partition 128 at 4 bits has no register left; its rank-1 operand is rebuilt for every tile
+  // from one (two prompts of 1999 tokens, 32/8 heads: 103.2 us with the operand kept, 98.8
+  // rebuilt; 2 bits, 237 to 252 registers, 91.1 and 93.2).  Left in scratch at partition 128,
+  // all but one reload of it outside the block loop: four to six registers at 4 bits to
+  // nearest and at 2 bits stochastically, none in the other variants.
   constexpr bool kRebuild = PI == 128 && BITS == 4;
   float rank_f[P];
   u32x4 rank_b[P], scale_b[P];
