@@ -441,12 +441,12 @@ __global__ __launch_bounds__(kGroupThreads* KG, 2) void prefill_kernel(PrefillAr
   // ---- Q row: codes per partition (float32 metadata), in MFMA operand layout: this lane
   // holds channels [p PI + half PI/2, + PI/2) of each partition p ----
   v4i qop[P][NJ];
-  // Partition 128 at 4 bits has no register left; its rank-1 operand is rebuilt for every tile
-  // from one (two prompts of 1999 tokens, 32/8 heads: 103.2 us with the operand kept, 98.8
-  // rebuilt; 2 bits, 237 to 252 registers, 91.1 and 93.2).  Left in scratch at partition 128,
-  // all but one reload of it outside the block loop: four to six registers at 4 bits to
-  // nearest and at 2 bits stochastically, none in the other variants.
-  constexpr bool kRebuild = PI == 128 && BITS == 4;
+  // Partition 128 has no register left at 4 bits or with stochastic codes; its rank-1 operand is
+  // rebuilt for every tile from one (two prompts of 1999 tokens, 32/8 heads: 4 bits 103.2 us with
+  // the operand kept, 98.8 rebuilt; 2 bits stochastic 223.3 and 219.2; but 2 bits to nearest,
+  // 246 to 252 registers, 91.1 and 93.2).  Left in scratch: four to six registers at 4 bits to
+  // nearest, all but one reload of them outside the block loop.
+  constexpr bool kRebuild = PI == 128 && (BITS == 4 || SR);
   float rank_f[P];
   u32x4 rank_b[P], scale_b[P];
   {
