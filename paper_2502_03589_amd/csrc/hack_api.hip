@@ -364,7 +364,7 @@ hack_status hack_attend_prefill(const hack_kv_layout* layout, const hack_kv_cach
   const hack_status sh = attention_shape(layout, num_q_heads);
   if (sh != HACK_OK) return sh;
   if (layout->sum_bytes == 0) return HACK_ERR_UNSUPPORTED;  // prefill reads cached sums
-  if (batch > kMaxGridYZ) return HACK_ERR_UNSUPPORTED;  // one grid plane per sequence
+  if (batch > kMaxGridYZ) return HACK_ERR_UNSUPPORTED;  // the largest batch of every call
   const int64_t cap = cache_capacity(layout, cache, batch);
   if (cap < 0) return HACK_ERR_INVALID_ARGUMENT;
   if (len > cap) return HACK_ERR_CAPACITY;
@@ -385,7 +385,7 @@ hack_status hack_project_qkv(const hack_kv_layout* layout, const hack_kv_cache* 
   if (cap < 0) return HACK_ERR_INVALID_ARGUMENT;
   if (len > cap) return HACK_ERR_CAPACITY;
   const int64_t tiles = (int64_t)batch * ((len + 255) / 256) * ((num_q_heads + 2 * layout->num_kv_heads + 1) / 2);
-  if (tiles > INT32_MAX) return HACK_ERR_UNSUPPORTED;  // one workgroup per tile in a 1-D grid
+  if (tiles > INT32_MAX) return HACK_ERR_UNSUPPORTED;  // workgroups of the largest tile shape
   if (batch == 0 || len == 0) return HACK_OK;
   hack::ProjectArgs a;
   std::memset(&a, 0, sizeof(a));

@@ -17,13 +17,13 @@
 //              products, so its steps are twice as deep (250 tokens, hidden 4096: 32.9 us
 //              with 32 channels a step, 28.3 with 64; one 256 x 256 tile per head pair 106).
 //   epilogue   the tile is rounded to fp16 into the stage buffers; then, for each of its
-//              two heads: a query head is written out in fp16 (the prefill attention
+//              heads: a query head is written out in fp16 (the prefill attention
 //              quantizes Q itself); a key head is quantized per (token, partition) and a
 //              value head per (V block, channel) straight into the cache, with the same
 //              quantizer and element indices as hack_quantize, including the fp16 open
 //              V block.  The fp16 K and V never reach device memory.
 // Tiles are numbered so that the workgroups one XCD runs at a time share their E and
-// W tiles (groups of four token tiles per channel tile, contiguous ranges per XCD), so
+// W tiles (groups of 1024 tokens per channel tile, contiguous ranges per XCD), so
 // each slab is fetched into that XCD's L2 once for several workgroups.
 #include "hack_internal.hpp"
 #include "launch_rules.hpp"

@@ -1,5 +1,5 @@
-"""GPU parity at the largest batch the launch grids take: decode and prefill run one
-grid row (decode) or plane (prefill) per sequence, so batch 65535 is the largest call.
+"""GPU parity at the largest batch the calls take: decode runs one grid row per sequence, so
+65535 is the largest, and prefill takes no more.
 Short ragged contexts keep the caches small; sampled sequences, the first and the last
 among them, are compared with the oracle at max|d| <= 2e-3 * max|O|."""
 import numpy as np
